@@ -87,6 +87,40 @@ def test_loss_and_gradient_match_oracle(d, b, h, dtype, gpu):
         assert rel <= 1e-4, name
 
 
+# (d, b, h, chunks of the mini-batch, dtype, element offset of the chunks'
+# base): one chunk; one fewer and one more than a 256-chunk tile; more tiles
+# than the per-chunk kernels have blocks; odd hidden widths; the widths whose
+# records take the 128-, 64- and 32-chunk tiles; chunks that are not 16-byte
+# aligned. The sums are trees over at most two tiles per block, shorter than
+# the chains the module's bar allows.
+@pytest.mark.parametrize("d,b,h,n,dtype,off", [
+    (8, 8, 8, 1, torch.bfloat16, 0), (8, 8, 5, 255, torch.bfloat16, 0), (8, 8, 8, 257, torch.float32, 1),
+    (8, 8, 8, 262221, torch.bfloat16, 0), (16, 16, 16, 1000, torch.bfloat16, 3), (16, 8, 33, 515, torch.float32, 0),
+    (16, 16, 64, 300, torch.bfloat16, 0), (8, 16, 1, 130, torch.bfloat16, 1)])
+def test_loss_and_gradient_at_tile_edges(d, b, h, n, dtype, off, gpu):
+    say(f"train grad d={d} b={b} h={h} n={n} {dtype} offset {off}")
+    cfg = bsq.Config(d=d, codebook_bits=b, hidden=h, encoder=bsq.ENC_LINEAR)
+    hp = bsq.TrainHyper(**HP)
+    flat = _stack(1, 512, 4096, seed=80 + h, dtype=dtype).reshape(-1).to(gpu)
+    W = flat[off:off + (flat.numel() - off) // d * d]
+    assert (W.data_ptr() % 16 == 0) == (off == 0)
+    idx = torch.randint(0, W.numel() // d, (n,), generator=torch.Generator().manual_seed(8), dtype=torch.int64)
+    theta = torch.from_numpy(_theta0(d, b, h, seed=61).astype(np.float32))
+    loss, grad = bsq.bsq_train_grad(cfg, hp, W, theta.to(gpu), idx=idx.to(gpu))
+    torch.cuda.synchronize()
+    X = oracle.to_f32(W.cpu().reshape(-1, d))[idx.numpy()]
+    ref, g_ref = OT.loss_and_grad(theta.numpy().astype(np.float64), X, d, b, h, OT.Hyper(**HP))
+    ent_mag = b * np.log(2.0) * (1.0 + HP["gamma"])
+    mags = (abs(ref[0]) + HP["lambda_e"] * ent_mag, abs(ref[1]), abs(ref[2]), ent_mag)
+    for k, (a, r, mag) in enumerate(zip(loss.cpu().numpy().astype(np.float64), ref, mags)):
+        assert abs(a - r) <= 1e-5 * mag, (k, a, r)
+    gg = grad.cpu().numpy().astype(np.float64)
+    for name, sl in zip(("E", "W1", "b1", "W2", "b2"), _blocks(d, b, h)):
+        rel = np.linalg.norm(gg[sl] - g_ref[sl]) / max(np.linalg.norm(g_ref[sl]), 1e-30)
+        say(f"  {name}: |grad - ref| / |ref| = {rel:.2e}")
+        assert rel <= 1e-4, name
+
+
 def test_out_of_range_index_is_reported_and_safe(gpu):
     cfg = bsq.Config(d=8, hidden=8, encoder=bsq.ENC_LINEAR)
     W = _stack(1, 64, 64, seed=3, dtype=torch.float32).to(gpu)
