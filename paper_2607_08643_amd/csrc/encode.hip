@@ -87,6 +87,132 @@ __global__ __launch_bounds__(256) void colscore_kernel(const T *__restrict__ W, 
     if (err && !__builtin_isfinite(s)) atomicOr(err, int32_t(BSQ_DEVERR_NONFINITE));
 }
 
+// The same scores for column counts that leave most of the chip idle with one
+// lane per column: there a wave has its own 64 rows (8 KiB) in flight and
+// converts, squares and compares between its loads (12288 x 4096 bf16, 64
+// waves: 261 us). Here a workgroup owns 64 columns and its eight waves take
+// 8 KiB tiles of the rows in turn. A wave brings its next two tiles to LDS by
+// DMA and reads, converts and compares a tile ahead of its turn; in its turn it
+// takes the 64 running sums from LDS, adds the tile, one fp64 fma a row (1.9
+// ns; with the conversion in the chain it would be 5.3), and hands the sums on.
+// The square of a bf16 or fp32 value is exact in fp64, so the fma rounds once,
+// as the separate product and sum do; rows past d_out are zeros, which change
+// neither the sum nor the absmax. Every wave of a workgroup is resident and
+// reaches each of its turns, so the wait for a turn ends.
+constexpr int SCT_WAVES = 8, SCT_SLOT = 80 * 128;
+
+template <typename T>
+__global__ __launch_bounds__(64 * SCT_WAVES) void colscore_turns_kernel(const T *__restrict__ W, int64_t d_out,
+                                                                       int64_t d_in, const float *__restrict__ g,
+                                                                       double *__restrict__ keys,
+                                                                       float *__restrict__ absmax, int32_t *err)
+{
+    constexpr int RB = 64 * int(sizeof(T)), R = SCT_SLOT / RB;  // bytes of a row's 64 columns, rows of a tile
+    constexpr int UPR = RB / 16, RPI = 64 / UPR;                // 16-byte units per row, rows per DMA instruction
+    constexpr int NI = R / RPI;                                 // DMA instructions per tile
+    constexpr int EPU = 16 / int(sizeof(T));
+    extern __shared__ __attribute__((aligned(16))) uint8_t s_slots[];  // [SCT_WAVES] tiles
+    __shared__ double s_sum[64];
+    __shared__ float s_max[SCT_WAVES][64];
+    __shared__ int s_turn;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t m = blockIdx.y, col0 = int64_t(blockIdx.x) * 64;
+    // this lane's 16-byte unit of a row (units past the row's end reload its last one; their sums are dropped)
+    int64_t cu = col0 + (lane % UPR) * EPU;
+    cu = (cu + EPU <= d_in) ? cu : d_in - EPU;
+    const T *base = W + m * d_out * d_in + cu;
+    const int rows = int(d_out), ntile = (rows + R - 1) / R;
+    uint8_t *slot = s_slots + wave * SCT_SLOT;
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const uint32_t sum_at = uint32_t(uintptr_t((lds_ptr)(s_sum + lane)));
+    const uint32_t turn_at = uint32_t(uintptr_t((lds_ptr)(&s_turn)));
+    auto dma = [&](int tile) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            int row = tile * R + i * RPI + lane / UPR;  // (rows past the end reload the last one)
+            row = (row < rows) ? row : rows - 1;
+            __builtin_amdgcn_global_load_lds(
+                reinterpret_cast<const uint4 *>(base + uint64_t(uint32_t(row)) * uint32_t(d_in)),
+                reinterpret_cast<uint4 *>(slot + i * 1024), 16, 0, 0);
+        }
+    };
+    dma(wave);
+    if (t == 0) s_turn = 0;
+    if (t < 64) s_sum[t] = 0.0;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    float mx = 0.0f;
+    const T *sp = reinterpret_cast<const T *>(slot) + lane;
+    for (int tile = wave; tile < ntile; tile += SCT_WAVES) {
+        __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));  // vmcnt(0): the tile is in LDS
+        asm volatile("" ::: "memory");
+        // eight rows' LDS reads ahead of the eight being converted
+        constexpr int U = 8;
+        T v[2][U];
+        double dv[R];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[0][u] = sp[u * 64];
+#pragma unroll
+        for (int b = 0; b < R / U; ++b) {
+            if (b + 1 < R / U) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[(b + 1) & 1][u] = sp[((b + 1) * U + u) * 64];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = b * U + u;
+                float f = load_elem<T>(&v[b & 1][u]);
+                f = (tile * R + r < rows) ? f : 0.0f;
+                mx = __builtin_fmaxf(mx, __builtin_fabsf(f));
+                dv[r] = double(f);
+                asm volatile("" : "+v"(dv[r]));  // (converted here, not in the wave's turn)
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // the slot's reads are done
+        asm volatile("" ::: "memory");
+        dma(tile + SCT_WAVES);
+        // this tile's turn, and the sums that the tile before left: read in
+        // that order in one round trip, with the wait in the same block (the
+        // compiler would wait for the DMAs before reading LDS)
+        double s;
+        int turn;
+        do {
+            asm volatile("ds_read_b32 %0, %2\n\tds_read_b64 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(turn), "=&v"(s)
+                         : "v"(turn_at), "v"(sum_at)
+                         : "memory");
+            turn = __builtin_amdgcn_readfirstlane(turn);
+            if (tile - turn > 1) __builtin_amdgcn_s_sleep(1);
+        } while (turn != tile);
+        __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+        for (int r = 0; r < R; ++r) s = __builtin_fma(dv[r], dv[r], s);
+        // (a wave's LDS operations are carried out in order: the sums are
+        // there before the turn changes)
+        asm volatile("ds_write_b64 %1, %0\n\tds_write_b32 %3, %2"
+                     :
+                     : "v"(s), "v"(sum_at), "v"(tile + 1), "v"(turn_at)
+                     : "memory");
+        __builtin_amdgcn_s_setprio(0);
+    }
+    s_max[wave][lane] = mx;
+    __syncthreads();  // (and no DMA is in flight into LDS past here)
+    const int64_t col = col0 + lane;
+    if (wave != 0 || col >= d_in) return;
+    double s = s_sum[lane];
+#pragma unroll
+    for (int w = 1; w < SCT_WAVES; ++w) mx = __builtin_fmaxf(mx, s_max[w][lane]);
+    if (g) {
+        double gj = double(g[m * d_in + col]);
+        s = (gj * gj) * s;
+    }
+    keys[m * d_in + col] = s;
+    absmax[m * d_in + col] = mx;
+    if (err && !__builtin_isfinite(s)) atomicOr(err, int32_t(BSQ_DEVERR_NONFINITE));
+}
+
 // ---------------------------------------------------------------------------
 // Row energy key_i = g_i^2 * sum_j w_ij^2 (fp64, columns in order) and the
 // row absmax: the output-channel score, and the gate/up terms of the coupled
@@ -198,8 +324,15 @@ __device__ int block_exclusive_scan(int v, int *s_wave, int &total)
 // protected columns. One block per matrix: an MSB-first radix select over the
 // 64-bit key patterns (non-negative doubles order like their bit patterns)
 // finds the k-th largest key T; then all keys > T and the lowest-index keys
-// equal to T are compacted in column order.
+// equal to T are compacted in column order. Latency is what bounds it (one
+// workgroup, a few barriers a digit): a thread keeps its run of up to KPT
+// consecutive keys in registers for the whole selection (KPT = 0: longer runs,
+// read again for every digit), a wave whose keys all fall into one bin adds
+// them in one atomic (the leading digits, the exponent, are mostly one or two
+// bins), and the selection ends at the first digit whose bin is wanted whole.
+// 4096 columns: 21.5 us before these, 9.8 us with them.
 // ---------------------------------------------------------------------------
+template <int KPT>
 __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__restrict__ keys_all,
                                                             const float *__restrict__ absmax_all,
                                                             int64_t d_in, int64_t k, int64_t words, float pmax,
@@ -213,6 +346,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
     __shared__ unsigned long long s_prefix;
     __shared__ long long s_remaining, s_next_remaining;
     __shared__ int s_wave[TOPK_THREADS / 64 + 1];
+    __shared__ int s_whole;
 
     const int64_t m = blockIdx.x;
     const int t = threadIdx.x;
@@ -223,9 +357,28 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
     int32_t *colmap = colmap_all + m * d_in;
     uint32_t *bitmap = bitmap_all + m * words;
 
+    // each thread owns a contiguous run of columns, so scans follow column order
+    const int64_t per = (d_in + TOPK_THREADS - 1) / TOPK_THREADS;
+    const int64_t j0 = t * per, j1 = (j0 + per < d_in) ? j0 + per : d_in;
+    unsigned long long kreg[KPT > 0 ? KPT : 1];
+    if constexpr (KPT > 0) {
+#pragma unroll
+        for (int i = 0; i < KPT; ++i) kreg[i] = (j0 + i < j1) ? keys[j0 + i] : 0ull;
+    }
+    // f(i, key) for the thread's columns j0 + i, in order
+    auto each = [&](auto f) {
+        if constexpr (KPT > 0) {
+#pragma unroll
+            for (int i = 0; i < KPT; ++i)
+                if (j0 + i < j1) f(i, kreg[i]);
+        } else {
+            for (int64_t j = j0; j < j1; ++j) f(int(j - j0), keys[j]);
+        }
+    };
     if (t == 0) {
         s_prefix = 0ull;
         s_remaining = k;
+        s_whole = 0;
     }
     unsigned long long mask = 0ull;
     for (int pass = 0; pass < 8; ++pass) {
@@ -233,10 +386,17 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
         for (int b = t; b < 256; b += TOPK_THREADS) hist[b] = 0u;
         __syncthreads();
         const unsigned long long prefix = s_prefix;
-        for (int64_t j = t; j < d_in; j += TOPK_THREADS) {
-            unsigned long long u = keys[j];
-            if ((u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 255ull], 1u);
-        }
+        each([&](int, unsigned long long u) {
+            if ((u & mask) != prefix) return;
+            const uint32_t bin = uint32_t(u >> shift) & 255u;
+            const uint32_t first = __builtin_amdgcn_readfirstlane(bin);
+            const unsigned long long same = __ballot(bin == first);  // of the lanes that are here
+            if (same == __ballot(1)) {
+                if ((t & 63) == __builtin_ctzll(same)) atomicAdd(&hist[first], uint32_t(__builtin_popcountll(same)));
+            } else {
+                atomicAdd(&hist[bin], 1u);
+            }
+        });
         __syncthreads();
         // the digit holding the rem-th largest key: with cum(dgt) the count of
         // keys in digits above dgt, the unique dgt with cum < rem <= cum + h.
@@ -261,42 +421,42 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
             if (cum < rem && rem <= (long long)incl) {
                 s_prefix = prefix | (static_cast<unsigned long long>(255 - t) << shift);
                 s_next_remaining = rem - cum;
+                s_whole = (rem - cum == (long long)h);  // every key of the bin is wanted
             }
         }
         __syncthreads();
         if (t == 0) s_remaining = s_next_remaining;
         mask |= 255ull << shift;
         __syncthreads();
+        if (s_whole) break;  // (uniform; written next after two more barriers)
     }
+    // the digits decided so far: keys above T are in, of those equal to it
+    // the first need_eq in column order
     const unsigned long long T = s_prefix;
     const long long need_eq = s_remaining;
-
-    // each thread owns a contiguous run of columns, so scans follow column order
-    const int64_t per = (d_in + TOPK_THREADS - 1) / TOPK_THREADS;
-    const int64_t j0 = t * per, j1 = (j0 + per < d_in) ? j0 + per : d_in;
     int n_eq = 0;
-    for (int64_t j = j0; j < j1; ++j) n_eq += (keys[j] == T);
+    each([&](int, unsigned long long u) { n_eq += ((u & mask) == T); });
     int tot;
     int eq_rank = block_exclusive_scan(n_eq, s_wave, tot);
     int n_sel = 0;
     {
         int r = eq_rank;
-        for (int64_t j = j0; j < j1; ++j) {
-            unsigned long long u = keys[j];
-            bool sel = (u > T) || (u == T && r < need_eq);
-            if (u == T) ++r;
-            n_sel += sel;
-        }
+        each([&](int, unsigned long long u) {
+            const unsigned long long um = u & mask;
+            n_sel += (um > T) || (um == T && r < need_eq);
+            if (um == T) ++r;
+        });
     }
     int pos = block_exclusive_scan(n_sel, s_wave, tot);
     for (int64_t w = t; w < words; w += TOPK_THREADS) s_bits[w] = 0u;
     __syncthreads();
     {
         int r = eq_rank;
-        for (int64_t j = j0; j < j1; ++j) {
-            unsigned long long u = keys[j];
-            bool sel = (u > T) || (u == T && r < need_eq);
-            if (u == T) ++r;
+        each([&](int i, unsigned long long u) {
+            const int64_t j = j0 + i;
+            const unsigned long long um = u & mask;
+            const bool sel = (um > T) || (um == T && r < need_eq);
+            if (um == T) ++r;
             if (sel) {
                 idx[pos] = int32_t(j);
                 scale[pos] = absmax[j] / pmax;
@@ -306,10 +466,26 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
             } else {
                 colmap[j] = -1;
             }
-        }
+        });
     }
     __syncthreads();
     for (int64_t w = t; w < words; w += TOPK_THREADS) bitmap[w] = s_bits[w];
+}
+
+hipError_t launch_topk(int64_t n_mats, const double *keys, const float *absmax, int64_t n, int64_t k, int64_t words,
+                       float pmax, int32_t *idx, float *scale, int32_t *colmap, uint32_t *bitmap, hipStream_t st)
+{
+    const dim3 grid(unsigned(n_mats), 1u, 1u), blk(TOPK_THREADS);
+    if (n <= 8 * TOPK_THREADS)
+        hipLaunchKernelGGL(topk_kernel<8>, grid, blk, size_t(words) * 4, st, keys, absmax, n, k, words, pmax, idx, scale,
+                           colmap, bitmap);
+    else if (n <= 32 * TOPK_THREADS)
+        hipLaunchKernelGGL(topk_kernel<32>, grid, blk, size_t(words) * 4, st, keys, absmax, n, k, words, pmax, idx,
+                           scale, colmap, bitmap);
+    else
+        hipLaunchKernelGGL(topk_kernel<0>, grid, blk, size_t(words) * 4, st, keys, absmax, n, k, words, pmax, idx, scale,
+                           colmap, bitmap);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -466,6 +642,30 @@ __device__ __forceinline__ void encode_fetch(const EncodeArgs &a, int64_t m, int
     if (a.bitmap) in.pmw = a.bitmap[m * a.words + ((c * D) >> 5)];
 }
 
+// A 16-byte load of data read once, which leaves L2 to the decoder tables.
+__device__ __forceinline__ uint4 load_stream(const uint4 *p)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
+// Lanes 2 p and 2 p + 1 hold the halves of one chunk in v[0] and of another in
+// v[1] (the even lane the first halves). Afterwards the even lane holds the
+// first chunk and the odd lane the second.
+__device__ __forceinline__ void pair_halves(uint4 (&v)[2], int odd)
+{
+    uint32_t *a = reinterpret_cast<uint32_t *>(&v[0]), *b = reinterpret_cast<uint32_t *>(&v[1]);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t give = odd ? a[w] : b[w];
+        const uint32_t got = uint32_t(__builtin_amdgcn_mov_dpp(int(give), 0xB1, 0xf, 0xf, true));  // lane ^ 1
+        const uint32_t lo = odd ? got : a[w], hi = odd ? b[w] : got;
+        a[w] = lo;
+        b[w] = hi;
+    }
+}
+
 template <int D, int B, int S, typename T, bool ENC>
 __device__ __forceinline__ void encode_element(const EncodeArgs &a, const float *s_tab, const float *s_E,
                                                int64_t m, int64_t i, int64_t c, int64_t gid, const ChunkIn<D, T> &in)
@@ -566,7 +766,12 @@ __device__ __forceinline__ void encode_element(const EncodeArgs &a, const float 
 // tables (d = 8) are staged in LDS once per block, and a tile's matrix, row
 // group and column block come from one scalar division per tile. Thread t
 // takes elements t, t + 256, ... of the tile: a wave covers four rows of 16
-// consecutive chunks, so its row reads are contiguous.
+// consecutive chunks, so its row reads are contiguous. bf16 chunks of 16
+// (32 bytes) are loaded as whole contiguous kilobytes, two lanes a chunk, and
+// the halves exchanged between the lanes: no line is read twice, so the loads
+// can pass L1 by and leave L2 to the decoder tables (4 MiB a stage), whose
+// entries the chunks gather. 8 x 4096 x 4096 at two stages: 248 us against 270
+// with each lane loading its own 32 bytes; the gathers alone take 146 us.
 template <int D, int B, int S, typename T, bool ENC>
 __global__ __launch_bounds__(256) void encode_kernel(EncodeArgs a)
 {
@@ -595,14 +800,32 @@ __global__ __launch_bounds__(256) void encode_kernel(EncodeArgs a)
         const int64_t rem = tile - m * tiles_per_mat;
         const int64_t rg = rem / nb, blk = rem - rg * nb;
         ChunkIn<D, T> in[4];
+        constexpr bool PAIR = D == 16 && sizeof(T) == 2;
+        // PAIR: even lanes own elements e0 + lane / 2, odd lanes those 32 further on
+        const int lane = int(threadIdx.x) & 63;
+        const int own = PAIR ? (int(threadIdx.x) & ~63) + (lane >> 1) + ((lane & 1) << 5) : int(threadIdx.x);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int e = q * 256 + int(threadIdx.x);
-            encode_fetch<D, T>(a, m, rg * 64 + (e >> 4), blk * 16 + (e & 15), in[q]);
+            const int e = q * 256 + own;
+            if constexpr (PAIR) {
+                const int e0 = q * 256 + (int(threadIdx.x) & ~63) + (lane >> 1);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {  // (past the matrix: a real chunk beside it, dropped)
+                    const int64_t i = rg * 64 + ((e0 + 32 * h) >> 4), c = blk * 16 + (e0 & 15);
+                    const T *src = static_cast<const T *>(a.W) + (m * a.d_out + ((i < a.d_out) ? i : a.d_out - 1)) * a.d_in +
+                                   ((c < a.C) ? c : a.C - 1) * D;
+                    in[q].raw[h] = load_stream(reinterpret_cast<const uint4 *>(src) + (lane & 1));
+                }
+                const int64_t c = blk * 16 + (e & 15);
+                in[q].pmw = (a.bitmap && c < a.C) ? a.bitmap[m * a.words + ((c * D) >> 5)] : 0u;
+            } else {
+                encode_fetch<D, T>(a, m, rg * 64 + (e >> 4), blk * 16 + (e & 15), in[q]);
+            }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int e = q * 256 + int(threadIdx.x);
+            const int e = q * 256 + own;
+            if constexpr (PAIR) pair_halves(in[q].raw, lane & 1);
             encode_element<D, B, S, T, ENC>(a, s_tab, s_E, m, rg * 64 + (e >> 4), blk * 16 + (e & 15), (tile << 10) + e,
                                             in[q]);
         }
@@ -723,10 +946,27 @@ size_t select_ws_layout(int64_t d_ffn, char *base, SelectWs *ws)
 
 namespace {
 
+// Up to this many 64-column groups the turns kernel is the faster one: 512
+// groups of 12288 rows 522 against 602 us for the whole encode, 2304 groups of
+// 4096 rows 752 against 766, 3072 groups of 4096 rows 1037 against 975 (there
+// one lane per column already keeps 12 waves a compute unit in flight).
+constexpr int64_t COLSCORE_TURNS_MAX_BLOCKS = 2560;
+
 template <typename T>
 hipError_t launch_colscore(const void *W, int64_t n_mats, int64_t d_out, int64_t d_in, const float *g, double *keys,
                            float *absmax, int32_t *err, hipStream_t st)
 {
+    const int64_t blocks = (d_in + 63) / 64 * n_mats;
+    // (it loads whole 16-byte units of rows that are there: none of an empty matrix)
+    if (d_out > 0 && d_out < (int64_t(1) << 30) && d_in * int64_t(sizeof(T)) % 16 == 0 && blocks <= COLSCORE_TURNS_MAX_BLOCKS) {
+        constexpr int lds = SCT_WAVES * SCT_SLOT;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&colscore_turns_kernel<T>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(colscore_turns_kernel<T>, dim3(unsigned((d_in + 63) / 64), unsigned(n_mats)),
+                           dim3(64 * SCT_WAVES), lds, st, static_cast<const T *>(W), d_out, d_in, g, keys, absmax, err);
+        return hipGetLastError();
+    }
     dim3 grid(unsigned((d_in + 255) / 256), unsigned(n_mats));
     hipLaunchKernelGGL(colscore_kernel<T>, grid, dim3(256), 0, st, static_cast<const T *>(W), d_out, d_in, g, keys,
                        absmax, err);
@@ -766,10 +1006,9 @@ hipError_t launch_encode(const bsq_config &cfg, const void *codec, const void *W
                                given, ws.absmax, d_in, k, words, payload_max(cfg.protect_format), out.prot_idx,
                                out.prot_scale, ws.colmap, out.prot_bits, err);
         else
-            hipLaunchKernelGGL(topk_kernel, dim3(unsigned(n_mats)), dim3(TOPK_THREADS), size_t(words) * 4, st,
-                               ws.keys, ws.absmax, d_in, k, words, payload_max(cfg.protect_format), out.prot_idx,
-                               out.prot_scale, ws.colmap, out.prot_bits);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+            e = launch_topk(n_mats, ws.keys, ws.absmax, d_in, k, words, payload_max(cfg.protect_format), out.prot_idx,
+                              out.prot_scale, ws.colmap, out.prot_bits, st);
+        if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
     }
     if (k > 0 && rows && !given) {
         // output-row scores and their TopK (indices to the layer; the scale,
@@ -778,10 +1017,9 @@ hipError_t launch_encode(const bsq_config &cfg, const void *codec, const void *W
                : launch_rowscore<float>(W, n_mats, d_out, d_in, g, ws.keys, ws.absmax, nullptr, st);
         if (e != hipSuccess) return e;
         const int64_t words = (d_out + 31) / 32;
-        hipLaunchKernelGGL(topk_kernel, dim3(unsigned(n_mats)), dim3(TOPK_THREADS), size_t(words) * 4, st, ws.keys,
-                           ws.absmax, d_out, k, words, payload_max(cfg.protect_format), out.prot_idx, out.prot_scale,
-                           ws.colmap, ws.bits);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        e = launch_topk(n_mats, ws.keys, ws.absmax, d_out, k, words, payload_max(cfg.protect_format), out.prot_idx,
+                        out.prot_scale, ws.colmap, ws.bits, st);
+        if (e != hipSuccess) return e;
     }
     EncodeArgs a{};
     a.W = W;
@@ -858,9 +1096,7 @@ hipError_t launch_coupled_select(const void *Wg, const void *Wu, const void *Wd,
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (k == 0) return hipSuccess;
     const int64_t words = (d_ffn + 31) / 32;
-    hipLaunchKernelGGL(topk_kernel, dim3(1u), dim3(TOPK_THREADS), size_t(words) * 4, st, ws.keys, ws.absmax, d_ffn, k,
-                       words, 127.0f, idx, ws.scale, ws.colmap, ws.bits);
-    return hipGetLastError();
+    return launch_topk(1, ws.keys, ws.absmax, d_ffn, k, words, 127.0f, idx, ws.scale, ws.colmap, ws.bits, st);
 }
 
 }  // namespace bsq

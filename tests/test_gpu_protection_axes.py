@@ -333,3 +333,58 @@ def test_row_axis_degenerate_cases(d, gpu):
             # every row protected: the planes hold only zeros
             for s in range(cfg.stages):
                 assert int(layer.codes[s].abs().sum()) == 0 and int(layer.gains[s].abs().sum()) == 0
+
+
+def _down_only_scores(W, gpu, cfg):
+    """Coupled scores and set of a down matrix alone (zero gate and up): the
+    square roots of its fp64 column sums."""
+    d_model, d_ffn = W.shape
+    Z = torch.zeros((d_ffn, d_model), dtype=W.dtype, device=gpu)
+    idx, sc = bsq.bsq_coupled_select(cfg, Z, Z, W.to(gpu), with_scores=True)
+    torch.cuda.synchronize()
+    return idx.cpu().numpy(), sc.cpu().numpy()
+
+
+# (rows, columns, dtype): one ragged tile and one column group; a tile of the
+# column sums (80 rows of bf16, 40 of fp32) less eight rows, whole and eight
+# more (the call takes whole chunks of rows); more tiles than a workgroup has
+# waves, and a ragged last one; columns that end
+# inside a 64-column group; rows that are not whole 16-byte units (the
+# one-lane-per-column kernel).
+@pytest.mark.parametrize("rows,cols,dtype", [
+    (8, 8, torch.bfloat16), (72, 64, torch.bfloat16), (80, 72, torch.bfloat16), (88, 136, torch.bfloat16),
+    (1304, 200, torch.bfloat16), (40, 12, torch.float32), (48, 68, torch.float32), (696, 132, torch.float32),
+    (96, 101, torch.bfloat16), (56, 33, torch.float32)])
+def test_column_sums_are_the_sequential_fp64_sums(rows, cols, dtype, gpu):
+    W, _ = synth.weight(rows, cols, seed=rows + cols, dtype=dtype)
+    W[:: max(1, rows // 3)] *= 2.0 ** -12  # rows whose squares round off
+    cfg = bsq.Config(protect_num=1, protect_den=10)
+    idx, sc = _down_only_scores(W, gpu, cfg)
+    w = W.float().numpy().astype(np.float64)
+    s = np.zeros(cols)
+    for i in range(rows):
+        s = s + w[i] * w[i]
+    assert np.array_equal(sc.view(np.int64), np.sqrt(s).view(np.int64))
+    ref = np.sort(np.argsort(-np.sqrt(s), kind="stable")[:cfg.k(cols)])
+    assert np.array_equal(idx, ref)
+
+
+# runs of the TopK in registers (up to 8 and 32 keys a thread) and read again
+# per digit; a set that ends at a bin border after one digit (two magnitudes),
+# inside a run of equal keys, and among random keys
+@pytest.mark.parametrize("n", [9, 1024, 8192, 8200, 32768, 40000])
+@pytest.mark.parametrize("kind", ["two", "equal", "random"])
+def test_topk_at_run_and_bin_edges(n, kind, gpu):
+    r = np.random.default_rng(n)
+    cfg = bsq.Config(protect_num=1, protect_den=100)
+    k = cfg.k(n)
+    v = np.ones(n, dtype=np.float32)
+    if kind == "two":
+        v[r.permutation(n)[:k]] = 1024.0
+    elif kind == "random":
+        v = r.normal(0, 1, n).astype(np.float32)
+    W = torch.zeros((8, n))
+    W[3] = torch.from_numpy(v)
+    idx, sc = _down_only_scores(W, gpu, cfg)
+    ref = np.sort(np.argsort(-np.abs(v).astype(np.float64), kind="stable")[:k])
+    assert np.array_equal(idx, ref)
