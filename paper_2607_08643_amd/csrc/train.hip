@@ -489,11 +489,21 @@ int64_t train_param_count(const bsq_config &cfg)
 
 int64_t train_record_floats(const bsq_config &cfg) { return 2 * cfg.d + 2 * int64_t(cfg.hidden) + 2 * cfg.b; }
 
+// The stated size (what a caller allocates, and the least that is accepted)
+// covers one record per chunk and a part sum per parameter of 512 groups. The
+// kernels keep the records in LDS and use less than that for every n: where
+// the back kernel has more than 512 blocks there are more than 512 x 32
+// chunks, whose records outweigh the further part sums.
 size_t train_ws_bytes(const bsq_config &cfg, int64_t n)
 {
+    const int64_t nblk = (n + TB - 1) / TB, P = train_param_count(cfg);
+    const size_t stated = align256(size_t(nblk) * cfg.b * 4) + align256(size_t(nblk) * 4) + 256 + 256 +
+                          align256(size_t(nblk) * 8) + align256(size_t(n) * train_record_floats(cfg) * 4) +
+                          align256(size_t(512) * P * 4);
     const TrainPlan p = train_plan(cfg, n);
-    return align256(size_t(p.nbits) * cfg.b * 4) + align256(size_t(p.nbits) * 4) + 256 + align256(size_t(p.nback) * 8) +
-           align256(size_t(p.nback) * train_param_count(cfg) * 4);
+    const size_t used = align256(size_t(p.nbits) * cfg.b * 4) + align256(size_t(p.nbits) * 4) + 256 +
+                        align256(size_t(p.nback) * 8) + align256(size_t(p.nback) * P * 4);
+    return std::max(stated, used);
 }
 
 hipError_t launch_train_grad(const bsq_config &cfg, const bsq_train_hparams &hp, const void *x, int x_dtype,
