@@ -461,13 +461,18 @@ bsq_status bsq_gemv_run(const bsq_config *cfg, int32_t n, const void *const *cod
  * eq. parallel_stage_decode, protected term of eq. protected_8bit_scatter,
  * LoRA term of Section III-F). Each lane decodes its weight fragments from
  * the code and gain planes straight into bf16 MFMA operands (fp16 decoder
- * tables in LDS, fp32 fma over the stages), so W_hat is never formed:
+ * tables in LDS, fp32 fma over the stages), so W_hat is never formed; for
+ * many tokens (above 64 at d = 16, above 256 at d = 8, fewer for many rows)
+ * and b = d the same bf16 weights are decoded once into the workspace and
+ * multiplied from there:
  *   X  device bf16 [M][ldx] (ldx >= d_in, multiple of 8)
  *   Y  device [M][ldy] of y_dtype (bf16 or fp32), ldy >= d_out
  *   ws device workspace of bsq_workspace_bytes(GEMM, 1, d_out, d_in, M),
  *      256-byte aligned, any contents: a 256-byte header the call leaves
  *      untouched, then scratch (X with the protected columns zeroed, the
- *      gathered protected activations, X A^T, split-K partials). One
+ *      gathered protected activations, X A^T, split-K partials, and for many
+ *      tokens up to 512 MiB of decoded weights; a workspace without room for
+ *      those is accepted, and the call then decodes per token tile). One
  *      workspace serves GEMM calls of any shape; calls that share it must
  *      not overlap.
  *   err device int32 error word or NULL (accepted for symmetry with

@@ -539,14 +539,14 @@ bsq_status bsq_gemm(const bsq_config *cfg, const void *codec, const bsq_layer *l
     if (!aligned(Y, y_dtype == BSQ_F32 ? 4 : 2)) return BSQ_ERR_ALIGN;
     if (err && !aligned(err, 4)) return BSQ_ERR_ALIGN;
     const bsq_config cc = coded_cfg(*cfg);
-    if (ws_bytes < gemm_ws_bytes(cc, layer->d_out, layer->d_in, M)) return BSQ_ERR_BUFFER_TOO_SMALL;
+    if (ws_bytes < gemm_ws_min_bytes(cc, layer->d_out, layer->d_in, M)) return BSQ_ERR_BUFFER_TOO_SMALL;
     const bool rows = row_axis(*cfg);
     if (!rows && layer->k > 4096) return BSQ_ERR_UNSUPPORTED;
     // the protected-row launch takes four tokens per block along grid y
     if (rows && (M + 3) / 4 > 65535) return BSQ_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bsq_layer coded = coded_layer(*cfg, *layer);
-    if ((s = from_hip(launch_gemm(cc, codec, coded, lora, X, M, ldx, Y, y_dtype, ldy, ws, err, st))) != BSQ_OK)
+    if ((s = from_hip(launch_gemm(cc, codec, coded, lora, X, M, ldx, Y, y_dtype, ldy, ws, ws_bytes, err, st))) != BSQ_OK)
         return s;
     if (!rows) return BSQ_OK;
     return from_hip(launch_gemm_rows(*layer, cfg->protect_format, lora, X, M, ldx, Y, y_dtype, ldy, gemm_lora_t(ws), st));

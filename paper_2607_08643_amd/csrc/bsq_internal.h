@@ -248,10 +248,23 @@ hipError_t launch_gemv_run(const bsq_config &cfg, int n, const void *const *code
 // whether a group's workspace fits the scratch array in its scratch layout
 bool gemv_scratch_fits(const bsq_config &cfg, int64_t n, int64_t max_d_out, int64_t d_in);
 
+// the workspace a call needs, and the one with which it takes its fastest path
+size_t gemm_ws_min_bytes(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M);
 size_t gemm_ws_bytes(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M);
 hipError_t launch_gemm(const bsq_config &cfg, const void *codec, const bsq_layer &layer,
                        const bsq_lora *lora, const void *X, int64_t M, int64_t ldx, void *Y,
-                       int y_dtype, int64_t ldy, void *ws, int32_t *err, hipStream_t st);
+                       int y_dtype, int64_t ldy, void *ws, size_t ws_bytes, int32_t *err, hipStream_t st);
+// Y = the sum of ks fp32 tiles part[ks][mp][np], in order (ks = 2 .. 8)
+hipError_t launch_splitk_sum(int ks, const float *part, int64_t mp, int64_t np, int64_t M, int64_t d_out, void *Y,
+                             int y_dtype, int64_t ldy, hipStream_t st);
+// The decode-once product for many tokens (gemm_dense.hip): whether it is the
+// faster one for a shape, its workspace (which launch_gemm uses it with, and
+// the call's other path without), its launch.
+bool gemm_dense_pays(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M);
+size_t gemm_dense_ws_bytes(int64_t d_out, int64_t d_in, int64_t M, int64_t k);
+hipError_t launch_gemm_dense(const bsq_config &cfg, const void *codec, const bsq_layer &layer, const bsq_lora *lora,
+                             const void *X, int64_t M, int64_t ldx, void *Y, int y_dtype, int64_t ldy, void *ws,
+                             hipStream_t st);
 
 // Codec training (train.hip): parameters of one stage codec, floats per chunk
 // record, workspace bytes for a batch of n chunks, and the two launches.

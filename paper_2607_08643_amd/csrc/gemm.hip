@@ -33,44 +33,10 @@
 #include <type_traits>
 
 #include "bsq_internal.h"
+#include "gemm_common.h"
 
 namespace bsq {
 namespace {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-constexpr int BK = 128;    // inputs per K step
-
-// The workspace starts with a 256-byte header that the product leaves
-// untouched (no block of it waits for another, so there is no poison word
-// or flagged slot to keep); the scratch of a call follows: T = X A^T, X~, the
-// gathered protected activations and the split-K partials.
-constexpr int64_t GEMM_HDR = 256;
-
-// Eight stored protected bytes (two words, byte e of the pair at bits
-// 8 (e % 4) of word e / 4) times their scales, in format FMT; the run-time
-// format is dispatched once per eight bytes (a uniform branch).
-template <int FMT>
-__device__ __forceinline__ void payload8_t(uint2 qv, const float *sc, float (&v)[8])
-{
-    v[0] = payload_byte<FMT, 0>(qv.x) * sc[0];
-    v[1] = payload_byte<FMT, 1>(qv.x) * sc[1];
-    v[2] = payload_byte<FMT, 2>(qv.x) * sc[2];
-    v[3] = payload_byte<FMT, 3>(qv.x) * sc[3];
-    v[4] = payload_byte<FMT, 0>(qv.y) * sc[4];
-    v[5] = payload_byte<FMT, 1>(qv.y) * sc[5];
-    v[6] = payload_byte<FMT, 2>(qv.y) * sc[6];
-    v[7] = payload_byte<FMT, 3>(qv.y) * sc[7];
-}
-
-__device__ __forceinline__ void payload8(uint2 qv, const float *sc, float (&v)[8], int fmt)
-{
-    if (fmt == BSQ_PROT_E4M3) payload8_t<BSQ_PROT_E4M3>(qv, sc, v);
-    else if (fmt == BSQ_PROT_E5M2) payload8_t<BSQ_PROT_E5M2>(qv, sc, v);
-    else payload8_t<BSQ_PROT_INT8>(qv, sc, v);
-}
 
 struct GemmArgs {
     const void *codes[BSQ_MAX_STAGES];
@@ -197,26 +163,6 @@ __global__ __launch_bounds__(256) void gemm_prep(const PrepArgs a)
 // ---------------------------------------------------------------------------
 // Main kernel.
 // ---------------------------------------------------------------------------
-
-// Workgroup barrier for LDS traffic only: waits for this wave's LDS (and
-// scalar) operations, not for its global loads, which stay in flight across
-// the barrier (__syncthreads would drain them with its release fence).
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), vmcnt and expcnt unconstrained
-    asm volatile("s_barrier" ::: "memory");
-}
-
-// Wait until at most N vector-memory operations of this wave are in flight.
-template <int N>
-__device__ __forceinline__ void wait_vm()
-{
-    static_assert(N >= 0 && N <= 63, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-// LDS of one workgroup (gfx950: 160 KiB per compute unit).
-constexpr int GEMM_LDS_BYTES = 160 * 1024;
 
 // Workgroups per compute unit of the main kernel. The 16-token, 64-row block
 // (56-74 VGPRs) runs three where three fit in LDS (4 ring slots of X~ and
@@ -918,6 +864,22 @@ __global__ __launch_bounds__(256) void gemm_splitk_sum(const GemmArgs a, int64_t
     }
 }
 
+hipError_t launch_sum(int ks, const GemmArgs &a, int64_t mp, hipStream_t st)
+{
+    const int64_t segs = a.M * ((a.d_out + 7) / 8);
+    const dim3 sg(unsigned((segs + 255) / 256));
+    switch (ks) {
+    case 2: hipLaunchKernelGGL(gemm_splitk_sum<2>, sg, dim3(256), 0, st, a, mp); break;
+    case 3: hipLaunchKernelGGL(gemm_splitk_sum<3>, sg, dim3(256), 0, st, a, mp); break;
+    case 4: hipLaunchKernelGGL(gemm_splitk_sum<4>, sg, dim3(256), 0, st, a, mp); break;
+    case 5: hipLaunchKernelGGL(gemm_splitk_sum<5>, sg, dim3(256), 0, st, a, mp); break;
+    case 6: hipLaunchKernelGGL(gemm_splitk_sum<6>, sg, dim3(256), 0, st, a, mp); break;
+    case 7: hipLaunchKernelGGL(gemm_splitk_sum<7>, sg, dim3(256), 0, st, a, mp); break;
+    default: hipLaunchKernelGGL(gemm_splitk_sum<8>, sg, dim3(256), 0, st, a, mp); break;
+    }
+    return hipGetLastError();
+}
+
 template <int D, int S, int MT, int NT>
 hipError_t launch_main(const GemmArgs &a, const GemmPlan &p, hipStream_t st)
 {
@@ -934,17 +896,7 @@ hipError_t launch_main(const GemmArgs &a, const GemmPlan &p, hipStream_t st)
     if (p.ksplit > 1) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int64_t segs = a.M * ((a.d_out + 7) / 8);
-        const dim3 sg(unsigned((segs + 255) / 256));
-        switch (p.ksplit) {
-        case 2: hipLaunchKernelGGL(gemm_splitk_sum<2>, sg, dim3(256), 0, st, a, p.Mp); break;
-        case 3: hipLaunchKernelGGL(gemm_splitk_sum<3>, sg, dim3(256), 0, st, a, p.Mp); break;
-        case 4: hipLaunchKernelGGL(gemm_splitk_sum<4>, sg, dim3(256), 0, st, a, p.Mp); break;
-        case 5: hipLaunchKernelGGL(gemm_splitk_sum<5>, sg, dim3(256), 0, st, a, p.Mp); break;
-        case 6: hipLaunchKernelGGL(gemm_splitk_sum<6>, sg, dim3(256), 0, st, a, p.Mp); break;
-        case 7: hipLaunchKernelGGL(gemm_splitk_sum<7>, sg, dim3(256), 0, st, a, p.Mp); break;
-        default: hipLaunchKernelGGL(gemm_splitk_sum<8>, sg, dim3(256), 0, st, a, p.Mp); break;
-        }
+        return launch_sum(int(p.ksplit), a, p.Mp, st);
     }
     return hipGetLastError();
 }
@@ -967,22 +919,52 @@ hipError_t launch_gemm_t(const GemmArgs &a, const GemmPlan &p, hipStream_t st)
 
 }  // namespace
 
+hipError_t launch_splitk_sum(int ks, const float *part, int64_t mp, int64_t np, int64_t M, int64_t d_out, void *Y,
+                             int y_dtype, int64_t ldy, hipStream_t st)
+{
+    GemmArgs a{};
+    a.part = const_cast<float *>(part);
+    a.np = np;
+    a.M = M;
+    a.d_out = d_out;
+    a.Y = Y;
+    a.ldy = ldy;
+    a.y_bf16 = (y_dtype == BSQ_BF16);
+    a.y_vec = (reinterpret_cast<uintptr_t>(Y) % 16 == 0) && ((ldy * (a.y_bf16 ? 2 : 4)) % 16 == 0);
+    return launch_sum(ks, a, mp, st);
+}
+
 const float *gemm_lora_t(const void *ws)
 {
     return reinterpret_cast<const float *>(static_cast<const char *>(ws) + GEMM_HDR);
 }
 
+static int64_t plan_k(const bsq_config &cfg, int64_t d_in)
+{
+    return cfg.protect_num ? (d_in * cfg.protect_num + cfg.protect_den - 1) / cfg.protect_den : 0;
+}
+
+size_t gemm_ws_min_bytes(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M)
+{
+    return gemm_plan(cfg.d, cfg.stages, d_out, d_in, M, plan_k(cfg, d_in)).total;
+}
+
 size_t gemm_ws_bytes(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M)
 {
-    const int64_t k = cfg.protect_num ? (d_in * cfg.protect_num + cfg.protect_den - 1) / cfg.protect_den : 0;
-    return gemm_plan(cfg.d, cfg.stages, d_out, d_in, M, k).total;
+    const size_t least = gemm_ws_min_bytes(cfg, d_out, d_in, M);
+    if (!gemm_dense_pays(cfg, d_out, d_in, M)) return least;
+    return std::max(least, gemm_dense_ws_bytes(d_out, d_in, M, plan_k(cfg, d_in)));
 }
 
 hipError_t launch_gemm(const bsq_config &cfg, const void *codec, const bsq_layer &L, const bsq_lora *lora,
                        const void *X, int64_t M, int64_t ldx, void *Y, int y_dtype, int64_t ldy, void *ws,
-                       int32_t *err, hipStream_t st)
+                       size_t ws_bytes, int32_t *err, hipStream_t st)
 {
     if (M == 0 || L.d_out == 0) return hipSuccess;
+    // a workspace of the smaller size stays on the path below
+    if (gemm_dense_pays(cfg, L.d_out, L.d_in, M) &&
+        ws_bytes >= gemm_dense_ws_bytes(L.d_out, L.d_in, M, L.k))
+        return launch_gemm_dense(cfg, codec, L, lora, X, M, ldx, Y, y_dtype, ldy, ws, st);
     const GemmPlan p = gemm_plan(cfg.d, cfg.stages, L.d_out, L.d_in, M, L.k);
     char *wb = static_cast<char *>(ws);
     GemmArgs a{};
