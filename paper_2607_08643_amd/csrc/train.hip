@@ -391,7 +391,7 @@ __global__ __launch_bounds__(TB) void train_back_kernel(const TrainArgs a)
 __global__ __launch_bounds__(TB) void train_sum_kernel(const TrainArgs a)
 {
     __shared__ float s_red[TB];
-    __shared__ float red[TB / 64 * 3];
+    __shared__ float red[TB / 64 * 2];
     const int t = threadIdx.x;
     if (blockIdx.x + 1 < gridDim.x) {
         const int64_t p = int64_t(blockIdx.x) * 16 + (t & 15);
@@ -411,18 +411,26 @@ __global__ __launch_bounds__(TB) void train_sum_kernel(const TrainArgs a)
         }
         return;
     }
-    float v[3] = {0.0f, 0.0f, 0.0f};  // reconstruction, commitment, entropy
+    // The entropy partials are added one after the other. L_ent is the small
+    // difference of two entropies near b ln 2, so the order of this sum shows
+    // in the loss (in a tree it moved by 6e-5 of itself at 131,072 chunks,
+    // b = 16): 512 additions from LDS, beside the other blocks' sums.
+    __shared__ float s_h[BITS_BLOCKS];
+    float v[2] = {0.0f, 0.0f};  // reconstruction, commitment
     for (int64_t k = t; k < a.nback; k += TB) {
         v[0] += a.l_part[2 * k];
         v[1] += a.l_part[2 * k + 1];
     }
-    for (int64_t k = t; k < a.nbits; k += TB) v[2] += a.h_part[k];
-    block_sums<3>(v, red);
+    for (int64_t k = t; k < a.nbits; k += TB) s_h[k] = a.h_part[k];
+    block_sums<2>(v, red);  // (its barriers also cover s_h)
     if (t == 0) {
+        float he = 0.0f;
+#pragma unroll 16
+        for (int k = 0; k < int(a.nbits); ++k) he += s_h[k];
         float bar_ent = 0.0f;
         for (int j = 0; j < a.b; ++j) bar_ent += entropy2(a.sbar[j]);
         const float inv_n = 1.0f / float(a.n);
-        const float L_rec = v[0] * inv_n, L_com = v[1] * inv_n, L_ent = v[2] * inv_n - a.gamma * bar_ent;
+        const float L_rec = v[0] * inv_n, L_com = v[1] * inv_n, L_ent = he * inv_n - a.gamma * bar_ent;
         a.loss[0] = L_rec + a.lambda_c * L_com + a.lambda_e * L_ent;
         a.loss[1] = L_rec;
         a.loss[2] = L_com;
