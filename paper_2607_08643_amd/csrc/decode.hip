@@ -25,7 +25,7 @@ struct DecodeArgs {
     int scatter;     // write the protected columns (the last stage of a sequential decode)
 };
 
-// A block walks the tiles of one matrix (grid-stride, so the decoder tables
+// A block walks tiles of one matrix (so the decoder tables
 // and the protected-column metadata are set up once per block). The four
 // threads 4 r .. 4 r + 3 share row r of the tile: each loads the row's 16
 // codes and gains of every stage (the four lanes read the same words) and
@@ -42,9 +42,20 @@ struct DecodeArgs {
 // below j (both kept in LDS), so no search over the list is needed.
 // D outputs per chunk, B code bits per stage (B = D unless the codec has a
 // linear encoder); the fp32 tables are in LDS for D = B = 8.
+//
+// Order of the tiles: with d = 8 and bf16 output a tile's row is 256 bytes of
+// W_hat, so blocks on different XCDs writing neighbouring tiles share cache
+// lines (always where a row is no multiple of 128 bytes). There a block takes
+// a run of neighbouring tiles: 11003 x 5000 in 42 us, 12288 x 4096 in 33
+// (strided by the grid: 53 and 47). With longer tile rows the strided order is
+// the faster one (d = 16 bf16 12288 x 4096: 88 us, in runs 100; d = 8 fp32
+// 11003 x 5000: 68 and 80).
+constexpr bool decode_runs(int d, bool bf16) { return d == 8 && bf16; }
+
 template <int D, int B, int S, bool BF16OUT>
 __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
 {
+    constexpr bool RUN = decode_runs(D, BF16OUT);
     constexpr bool TAB_LDS = (D == 8 && B == 8);
     extern __shared__ uint32_t s_mem[];
     // [words4] protected bitmap, [words4] rank of each word's first protected
@@ -165,7 +176,7 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
             if constexpr (BF16OUT) {
                 uint32_t h[D / 2];
 #pragma unroll
-                for (int j = 0; j < D / 2; ++j) h[j] = uint32_t(f32_to_bf16(v[2 * j])) | (uint32_t(f32_to_bf16(v[2 * j + 1])) << 16);
+                for (int j = 0; j < D / 2; ++j) h[j] = pack_bf16x2(v[2 * j], v[2 * j + 1]);
                 uint4 *dst = reinterpret_cast<uint4 *>(static_cast<uint16_t *>(a.out) + o);
 #pragma unroll
                 for (int q = 0; q < D / 8; ++q) dst[q] = make_uint4(h[4 * q], h[4 * q + 1], h[4 * q + 2], h[4 * q + 3]);
@@ -177,18 +188,19 @@ __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
             }
         }
     };
-    int64_t tile = blockIdx.x;
-    if (tile >= tiles) return;
+    int64_t tile = RUN ? tiles * blockIdx.x / gridDim.x : blockIdx.x;
+    const int64_t end = RUN ? tiles * (blockIdx.x + 1) / gridDim.x : tiles, step = RUN ? 1 : gridDim.x;
+    if (tile >= end) return;
     load(0, tile);
     for (;;) {
-        const int64_t t1 = tile + gridDim.x;
-        load(1, (t1 < tiles) ? t1 : tile);
+        const int64_t t1 = tile + step;
+        load(1, (t1 < end) ? t1 : tile);
         body(0, tile);
-        if (t1 >= tiles) break;
-        const int64_t t2 = t1 + gridDim.x;
-        load(0, (t2 < tiles) ? t2 : t1);
+        if (t1 >= end) break;
+        const int64_t t2 = t1 + step;
+        load(0, (t2 < end) ? t2 : t1);
         body(1, t1);
-        if (t2 >= tiles) break;
+        if (t2 >= end) break;
         tile = t2;
     }
 }
@@ -199,7 +211,10 @@ hipError_t launch_decode_t(int stages, const DecodeArgs &a, int64_t n_mats, hipS
     const int64_t tiles = (a.d_out + 63) / 64 * (a.pitch / 16);
     if (tiles == 0 || n_mats == 0) return hipSuccess;
     // about eight blocks per CU in all, each walking its share of the tiles
-    int64_t gx = (2048 + n_mats - 1) / n_mats;
+    // (four where a block walks neighbouring tiles: 1024, 1536 and 2048 blocks
+    // took 33, 34 and 38 us on 12288 x 4096)
+    const int64_t nblk = decode_runs(D, BF16OUT) ? 1024 : 2048;
+    int64_t gx = (nblk + n_mats - 1) / n_mats;
     if (gx > tiles) gx = tiles;
     if (gx < 1) gx = 1;
     const dim3 grid = dim3(unsigned(gx), unsigned(n_mats));

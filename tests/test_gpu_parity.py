@@ -639,3 +639,19 @@ def test_gemm_lora_and_protected_terms(d, M, fmt, gpu):
     lora, q8t, q8sq, total = _terms_ref(enc, w_hat, Xf, (oracle.to_f32(A), oracle.to_f32(Bm)), OFMT[fmt])
     assert term_bar(Y_l, Y_0, lora, total, 16, "LoRA term") > 100
     assert term_bar(Y_0, Y_m, q8t, total, len(enc.idx), "protected term", rounded=q8sq) > 10
+
+
+@pytest.mark.parametrize("n_mats,d_out,d_in", [(1, 1100, 9000), (3, 700, 4104), (1, 65, 131072)])
+def test_bf16_decode_in_tile_runs_equals_rounded_fp32(n_mats, d_out, d_in, gpu):
+    """d = 8 with bf16 output: more tiles than workgroups, in runs of uneven
+    length over ragged rows. Every element is the fp32 decode's (another tile
+    order) rounded to nearest even."""
+    say(f"bf16 decode runs {n_mats}x{d_out}x{d_in}")
+    cfg = bsq.Config(d=8, hidden=8)
+    codec = bsq.bsq_codec_prepare(cfg, decoders(cfg, seed=9), device=gpu)
+    W, _ = synth.weight(d_out, d_in, seed=13, k_outliers=cfg.k(d_in), device=gpu, n_mats=n_mats)
+    layer = bsq.bsq_encode(cfg, codec, W)
+    out = torch.full(W.shape, float("nan"), dtype=torch.bfloat16, device=gpu)
+    bsq.bsq_decode(cfg, codec, layer, out=out)
+    f32 = bsq.bsq_decode(cfg, codec, layer, out=torch.empty(W.shape, dtype=torch.float32, device=gpu))
+    assert torch.equal(out, f32.to(torch.bfloat16))
