@@ -37,6 +37,10 @@ typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 // at 2000 tokens took 362 us in two of them, 257 in one.
 constexpr int64_t DENSE_SLAB_BYTES = int64_t(512) << 20;
 
+// Decoded weights up to this size come from the last-level cache (256 MiB)
+// when the product reads them.
+constexpr int64_t DENSE_CACHED_BYTES = int64_t(224) << 20;
+
 struct DenseArgs {
     const void *codes[BSQ_MAX_STAGES];
     const uint16_t *gains[BSQ_MAX_STAGES];
@@ -517,17 +521,21 @@ DensePlan dense_plan(int64_t d_out, int64_t d_in, int64_t M, int64_t k)
     // Tile and K split with the least estimated time (us): rounds of blocks
     // over the 256 compute units, a unit step taking 0.13 + 0.56 per 256 x 256
     // of tile (0.28, 0.41, 0.59 and 0.68 measured for the four tiles on 4096
-    // inputs) and a block about 8 besides; the fp32 tiles of a split are
-    // written, read and added in a launch of its own.
+    // inputs; 128 x 128 tiles 8% more where the weights come from memory) and a
+    // block about 8 besides; the fp32 tiles of a split are written whole, read
+    // and added in a launch of its own. (Without the padded tokens and rows in
+    // that, 257 tokens of 2048 x 8192 took 256-token tiles in 8 splits: 51 us
+    // against 41; 129 tokens of 8192 x 4096 58 against 52.)
     double best = 1e300;
     for (int i = 0; i < 4; ++i) {
         const DenseTile &c = DENSE_TILES[i];
         const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((d_out + c.bn - 1) / c.bn);
         for (int ks : {1, 2, 3, 4, 6, 8}) {
             if (ks > 1 && (tiles * ks > 256 || p.KU / ks < 24 || p.nslab > 1)) break;
-            const double step = 0.13 + 0.56 * c.bm * c.bn / 65536.0;
+            const double step = (0.13 + 0.56 * c.bm * c.bn / 65536.0) * (c.bm == 128 && d_out * row_bytes > DENSE_CACHED_BYTES ? 1.08 : 1.0);
             const double us = double((tiles * ks + 255) / 256) * (double(p.KU) / ks * step + 8.0) +
-                              (ks > 1 ? 5.0 + double(M) * double(d_out) * (8.0 * ks + 2.0) / 4e6 : 0.0);
+                              (ks > 1 ? 5.0 + (4.0 * ks * double(tiles) * c.bm * c.bn + (4.0 * ks + 2.0) * double(M) * double(d_out)) / 4e6
+                                      : 0.0);
             if (us < best) {
                 best = us;
                 p.tile = i;
