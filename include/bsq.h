@@ -461,10 +461,13 @@ bsq_status bsq_gemv_run(const bsq_config *cfg, int32_t n, const void *const *cod
  * eq. parallel_stage_decode, protected term of eq. protected_8bit_scatter,
  * LoRA term of Section III-F). Each lane decodes its weight fragments from
  * the code and gain planes straight into bf16 MFMA operands (fp16 decoder
- * tables in LDS, fp32 fma over the stages), so W_hat is never formed; for
- * many tokens (above 64 at d = 16, above 256 at d = 8, fewer for many rows)
- * and b = d the same bf16 weights are decoded once into the workspace and
- * multiplied from there:
+ * tables in LDS, fp32 fma over the stages), so W_hat is never formed. For
+ * many tokens and b = d the same bf16 weights may be decoded once into the
+ * workspace and multiplied from there, where that is estimated to be faster:
+ * above 1024 tokens always, up to there above 64 (d = 16) or 256 (d = 8, and
+ * from 129 with d_out >= 4096 and d_in <= d_out), by shape, stages and tokens.
+ * Both ways round the same weights to bf16 and differ in the order of the
+ * fp32 sums only:
  *   X  device bf16 [M][ldx] (ldx >= d_in, multiple of 8)
  *   Y  device [M][ldy] of y_dtype (bf16 or fp32), ldy >= d_out
  *   ws device workspace of bsq_workspace_bytes(GEMM, 1, d_out, d_in, M),
@@ -472,9 +475,11 @@ bsq_status bsq_gemv_run(const bsq_config *cfg, int32_t n, const void *const *cod
  *      untouched, then scratch (X with the protected columns zeroed, the
  *      gathered protected activations, X A^T, split-K partials, and for many
  *      tokens up to 512 MiB of decoded weights; a workspace without room for
- *      those is accepted, and the call then decodes per token tile). One
- *      workspace serves GEMM calls of any shape; calls that share it must
- *      not overlap.
+ *      those is accepted as long as it holds the scratch of the call that
+ *      decodes per token tile, which then runs: its size is what is reported
+ *      for shapes that do not decode once, and a lower bound of every other
+ *      report). One workspace serves GEMM calls of any shape that it is large
+ *      enough for; calls that share it must not overlap.
  *   err device int32 error word or NULL (accepted for symmetry with
  *      bsq_gemv; no workgroup of the product waits for another, so nothing
  *      is reported).

@@ -257,10 +257,10 @@ hipError_t launch_gemm(const bsq_config &cfg, const void *codec, const bsq_layer
 // Y = the sum of ks fp32 tiles part[ks][mp][np], in order (ks = 2 .. 8)
 hipError_t launch_splitk_sum(int ks, const float *part, int64_t mp, int64_t np, int64_t M, int64_t d_out, void *Y,
                              int y_dtype, int64_t ldy, hipStream_t st);
-// The decode-once product for many tokens (gemm_dense.hip): whether it is the
-// faster one for a shape, its workspace (which launch_gemm uses it with, and
-// the call's other path without), its launch.
-bool gemm_dense_pays(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M);
+// The decode-once product for many tokens (gemm_dense.hip): its estimated time
+// (us), its workspace (which launch_gemm uses it with, and the call's other
+// path without), its launch.
+double gemm_dense_us(int d, int stages, int64_t d_out, int64_t d_in, int64_t M, int64_t k, int rank);
 size_t gemm_dense_ws_bytes(int64_t d_out, int64_t d_in, int64_t M, int64_t k);
 hipError_t launch_gemm_dense(const bsq_config &cfg, const void *codec, const bsq_layer &layer, const bsq_lora *lora,
                              const void *X, int64_t M, int64_t ldx, void *Y, int y_dtype, int64_t ldy, void *ws,

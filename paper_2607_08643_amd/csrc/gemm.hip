@@ -944,6 +944,57 @@ static int64_t plan_k(const bsq_config &cfg, int64_t d_in)
     return cfg.protect_num ? (d_in * cfg.protect_num + cfg.protect_den - 1) / cfg.protect_den : 0;
 }
 
+// Estimated time (us) of a call on this file's path: rounds of workgroups over
+// the compute units, each a block's K steps and its prologue and epilogue,
+// the split-K sum (a launch, and the partials written and read at 4 MB/us),
+// the preparation of X, the adapter.
+static double gemm_tiled_us(int d, int stages, int64_t d_out, int64_t d_in, int64_t M, int64_t k, int rank)
+{
+    const GemmPlan p = gemm_plan(d, stages, d_out, d_in, M, k);
+    struct Cost { double call, step, step_s, round, round_s, sum, sum_mb, x, rank; };
+    // d = 8: 128-token tiles of 64- and of 128-row blocks; d = 16: 128-, 256-token tiles
+    constexpr Cost C[] = {{0.0, 0.66, 0.17, 9.9, 0.04, 0.65, 0.56, 4.1, 5.2},
+                          {2.6, 1.22, 0.23, 7.2, 0.44, 4.3, 0.66, 1.5, 7.6},
+                          {0.0, 0.0, 2.72, 8.1, 1.25, 1.8, 1.3, 3.9, 4.3},
+                          {0.8, 2.4, 1.03, 8.6, 1.19, 1.0, 1.2, 2.0, 6.1}};
+    const Cost &c = C[d == 8 ? p.nt - 1 : (p.mt == 16 ? 3 : 2)];
+    const int64_t tiles = p.nblk * p.mtiles, slots = 256 * gemm_wg_per_cu(d, stages, p.mt, p.nt);
+    const double rounds = double((tiles * p.ksplit + slots - 1) / slots);
+    const double steps = double((p.ksteps + p.ksplit - 1) / p.ksplit);
+    const double part = 4.0 * double(p.ksplit) * (double(tiles) * double(p.bm * p.bn) + double(M) * double(d_out));
+    return c.call + rounds * (steps * (c.step + c.step_s * stages) + c.round + c.round_s * stages) +
+           (p.ksplit > 1 ? c.sum + c.sum_mb * part / 4e6 : 0.0) + c.x * double(M) * double(d_in) * 1e-6 +
+           (rank > 0 ? c.rank : 0.0);
+}
+
+// Whether decoding once (gemm_dense.hip) is the faster path. It is for many
+// tokens: at d = 8 above 256, from 129 where the rows are many and K is no
+// longer than they are; at d = 16, where the tiled path gathers every table
+// entry again for each token tile, above 64. Up to 1024 tokens the line
+// between them runs through those ranges with the tiled path's rounds of
+// blocks over the compute units (a full last round makes it fast), the stages
+// (the decode it repeats) and the size of the decoded weights (which the other
+// path writes and reads), so both times are estimated there. From replayed
+// graphs over rotated layers (tiled us -> decode-once us), rank 16:
+//   d = 8, 2 stages, 256 tokens: 12288 x 4096 73 -> 67, 18944 x 3584 122 -> 87,
+//   8192 x 8192 79 -> 91, 16384 x 8192 126 -> 180; 1 stage 25600 x 5120
+//   149 -> 161, 4 stages 212 -> 194; 320 tokens of 5120 x 25600 208 -> 220;
+//   d = 16, 96 tokens, 1 / 2 / 3 stages: 4096 x 12288 61 -> 78, 105 -> 110,
+//   127 -> 150; 12288 x 4096 65 -> 76, 119 -> 109, 148 -> 150; 2 stages
+//   1024 x 4096 42 -> 30.
+// The estimates choose the slower path by more than 2% in 3% of 4800 measured
+// cells (64 - 151936 rows, 256 - 28672 inputs, 1 - 4 stages, with and without
+// an adapter); the token bounds alone did in 12%, by up to 58%. The tiled path
+// has to win by 2%.
+static bool gemm_dense_pays(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M, int64_t k, int rank)
+{
+    if (cfg.b != cfg.d || d_out == 0) return false;
+    if (cfg.d == 16 ? M <= 64 : (M <= 128 || (M <= 256 && (d_out < 4096 || d_in > d_out)))) return false;
+    if (M > 1024) return true;
+    return gemm_dense_us(cfg.d, cfg.stages, d_out, d_in, M, k, rank) <
+           1.02 * gemm_tiled_us(cfg.d, cfg.stages, d_out, d_in, M, k, rank);
+}
+
 size_t gemm_ws_min_bytes(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M)
 {
     return gemm_plan(cfg.d, cfg.stages, d_out, d_in, M, plan_k(cfg, d_in)).total;
@@ -951,9 +1002,11 @@ size_t gemm_ws_min_bytes(const bsq_config &cfg, int64_t d_out, int64_t d_in, int
 
 size_t gemm_ws_bytes(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M)
 {
+    // (the adapter of the call is not known here)
+    const int64_t k = plan_k(cfg, d_in);
     const size_t least = gemm_ws_min_bytes(cfg, d_out, d_in, M);
-    if (!gemm_dense_pays(cfg, d_out, d_in, M)) return least;
-    return std::max(least, gemm_dense_ws_bytes(d_out, d_in, M, plan_k(cfg, d_in)));
+    if (!gemm_dense_pays(cfg, d_out, d_in, M, k, 0) && !gemm_dense_pays(cfg, d_out, d_in, M, k, BSQ_MAX_LORA_RANK)) return least;
+    return std::max(least, gemm_dense_ws_bytes(d_out, d_in, M, k));
 }
 
 hipError_t launch_gemm(const bsq_config &cfg, const void *codec, const bsq_layer &L, const bsq_lora *lora,
@@ -962,7 +1015,7 @@ hipError_t launch_gemm(const bsq_config &cfg, const void *codec, const bsq_layer
 {
     if (M == 0 || L.d_out == 0) return hipSuccess;
     // a workspace of the smaller size stays on the path below
-    if (gemm_dense_pays(cfg, L.d_out, L.d_in, M) &&
+    if (gemm_dense_pays(cfg, L.d_out, L.d_in, M, L.k, lora ? int(lora->rank) : 0) &&
         ws_bytes >= gemm_dense_ws_bytes(L.d_out, L.d_in, M, L.k))
         return launch_gemm_dense(cfg, codec, L, lora, X, M, ldx, Y, y_dtype, ldy, ws, st);
     const GemmPlan p = gemm_plan(cfg.d, cfg.stages, L.d_out, L.d_in, M, L.k);

@@ -506,6 +506,7 @@ struct DensePlan {
     int tile, ksplit;
     int64_t bm, bn, mtiles, Mp, ksteps, kp32, KU, slab, nslab;
     int nxseg;  // workgroups of 512 inputs along a row of X
+    double us;  // estimated time of the product
     size_t tp_off, xe_off, we_off, part_off, total;
 };
 
@@ -543,6 +544,7 @@ DensePlan dense_plan(int64_t d_out, int64_t d_in, int64_t M, int64_t k)
             }
         }
     }
+    p.us = best;
     p.bm = DENSE_TILES[p.tile].bm;
     p.bn = DENSE_TILES[p.tile].bn;
     p.mtiles = std::max<int64_t>((M + p.bm - 1) / p.bm, 1);
@@ -587,23 +589,20 @@ hipError_t launch_product(DenseArgs a, hipStream_t st)
 
 }  // namespace
 
-// Where decoding once is the faster path. Measured with a rank-16 adapter
-// (tiled path -> this one, us):
-//   d = 16, above 64 tokens (the tiled path gathers every table entry again
-//   for each token tile): 12288 x 4096 at 64 / 96 / 256 / 2000 tokens
-//   93 -> 99, 114 -> 99, 147 -> 108, 858 -> 254; 4096 x 12288 at 64 / 96 / 256
-//   81 -> 99, 101 -> 100, 134 -> 113; 64 x 4096 at 64 / 96 20 -> 27, 33 -> 27;
-//   d = 8, above 256 tokens: 12288 x 4096 at 264 / 2000 135 -> 80, 401 -> 204;
-//   4096 x 12288 113 -> 90, 455 -> 217; 1024 x 4096 at 264 32 -> 30; and from
-//   129 tokens where the rows are many and K is no longer than they are (the
-//   tiled path has too few blocks of 128 tokens there): 12288 x 4096 at 160
-//   76 -> 64, 4096 x 4096 39 -> 36; not 4096 x 12288 at 160 (69 -> 77) or
-//   1024 x 4096 at 256 (24 -> 29).
-bool gemm_dense_pays(const bsq_config &cfg, int64_t d_out, int64_t d_in, int64_t M)
+// The product's estimate scaled to a whole call, and the operands: decoding
+// the weights (written and read back through memory where they outgrow the
+// last-level cache), X, the adapter. Coefficients: per stage, of the product,
+// per million weights, of those per stage, of those past 60 million more, per
+// million elements of X, the adapter's launch. Fitted as gemm_tiled_us, which
+// says over what.
+double gemm_dense_us(int d, int stages, int64_t d_out, int64_t d_in, int64_t M, int64_t k, int rank)
 {
-    if (cfg.b != cfg.d) return false;
-    if (cfg.d == 16) return M > 64;
-    return M > 256 || (M > 128 && d_out >= 4096 && d_in <= d_out);
+    const double C8[] = {0.94, 0.76, 0.335, 0.084, 0.5, 0.91, 3.5};
+    const double C16[] = {3.3, 0.656, 0.142, 0.685, 0.34, 1.9, 2.75};
+    const double *c = (d == 8) ? C8 : C16;
+    const double w = double(d_out) * double(d_in) * 1e-6;
+    return c[0] * stages + c[1] * dense_plan(d_out, d_in, M, k).us + (c[2] + c[3] * stages) * w +
+           c[4] * std::max(0.0, w - 60.0) + c[5] * double(M) * double(d_in) * 1e-6 + (rank > 0 ? c[6] : 0.0);
 }
 
 size_t gemm_dense_ws_bytes(int64_t d_out, int64_t d_in, int64_t M, int64_t k)
