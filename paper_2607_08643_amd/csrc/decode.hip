@@ -46,16 +46,19 @@ struct DecodeArgs {
 // Order of the tiles: with d = 8 and bf16 output a tile's row is 256 bytes of
 // W_hat, so blocks on different XCDs writing neighbouring tiles share cache
 // lines (always where a row is no multiple of 128 bytes). There a block takes
-// a run of neighbouring tiles: 11003 x 5000 in 42 us, 12288 x 4096 in 33
-// (strided by the grid: 53 and 47). With longer tile rows the strided order is
-// the faster one (d = 16 bf16 12288 x 4096: 88 us, in runs 100; d = 8 fp32
-// 11003 x 5000: 68 and 80).
-constexpr bool decode_runs(int d, bool bf16) { return d == 8 && bf16; }
+// a run of neighbouring tiles: over rotated outputs 11003 x 5000 in 69 us,
+// 12288 x 4096 in 49 (strided by the grid: 76 and 54). With longer tile rows
+// the strided order is the faster one (d = 16 bf16 12288 x 4096: 88 us, in
+// runs 100; d = 8 fp32 11003 x 5000: 68 and 80; both repeated on one output),
+// and with one stage of 16-bit codes, which waits for the table's gathers
+// from L2 and not for the stores (12288 x 4096 62 us, in runs 67; two stages
+// 135 either way, a stack of 16 x 4096 x 4096 in runs 5% faster).
+constexpr bool decode_runs(int d, int b, int stages, bool bf16) { return d == 8 && bf16 && (b == 8 || stages > 1); }
 
 template <int D, int B, int S, bool BF16OUT>
 __global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a)
 {
-    constexpr bool RUN = decode_runs(D, BF16OUT);
+    constexpr bool RUN = decode_runs(D, B, S, BF16OUT);
     constexpr bool TAB_LDS = (D == 8 && B == 8);
     extern __shared__ uint32_t s_mem[];
     // [words4] protected bitmap, [words4] rank of each word's first protected
@@ -211,10 +214,19 @@ hipError_t launch_decode_t(int stages, const DecodeArgs &a, int64_t n_mats, hipS
     const int64_t tiles = (a.d_out + 63) / 64 * (a.pitch / 16);
     if (tiles == 0 || n_mats == 0) return hipSuccess;
     // about eight blocks per CU in all, each walking its share of the tiles
-    // (four where a block walks neighbouring tiles: 1024, 1536 and 2048 blocks
-    // took 33, 34 and 38 us on 12288 x 4096)
-    const int64_t nblk = decode_runs(D, BF16OUT) ? 1024 : 2048;
-    int64_t gx = (nblk + n_mats - 1) / n_mats;
+    int64_t gx = (2048 + n_mats - 1) / n_mats;
+    if (decode_runs(D, B, stages, BF16OUT)) {
+        // four where a block walks neighbouring tiles (1024, 1536 and 2048
+        // blocks took 33, 34 and 38 us on 12288 x 4096, repeated), and none
+        // left over for a round of its own: rounded up, 12 x 4096 x 4096 at
+        // two stages of 8-bit codes took 186 us against 178, of 16-bit codes
+        // 639 against 541. Runs of 4 KiB of a row start all blocks of a row
+        // group on the same memory channels, so they are halved (8-bit codes:
+        // 8 x 4096 x 4096 at 1 / 2 / 4 stages 141 / 131 / 165 us, halved
+        // 122 / 127 / 143; 16-bit codes gain nothing).
+        gx = 1024 / n_mats;
+        if (B == 8 && tiles == 16 * gx) gx *= 2;
+    }
     if (gx > tiles) gx = tiles;
     if (gx < 1) gx = 1;
     const dim3 grid = dim3(unsigned(gx), unsigned(n_mats));
