@@ -326,11 +326,13 @@ __device__ int block_exclusive_scan(int v, int *s_wave, int &total)
 // finds the k-th largest key T; then all keys > T and the lowest-index keys
 // equal to T are compacted in column order. Latency is what bounds it (one
 // workgroup, a few barriers a digit): a thread keeps its run of up to KPT
-// consecutive keys in registers for the whole selection (KPT = 0: longer runs,
-// read again for every digit), a wave whose keys all fall into one bin adds
-// them in one atomic (the leading digits, the exponent, are mostly one or two
-// bins), and the selection ends at the first digit whose bin is wanted whole.
-// 4096 columns: 21.5 us before these, 9.8 us with them.
+// consecutive keys in registers for the whole selection, a wave whose keys all
+// fall into one bin adds them in one atomic (the leading digits, the exponent,
+// are mostly one or two bins), and the selection ends at the first digit whose
+// bin is wanted whole. 4096 columns: 21.5 us before these, 9.8 us with them.
+// KPT = 0, for longer runs: the keys are read again for every digit, by
+// neighbouring lanes (an encode of 64 x 151936 in 494 us; 643 with each thread
+// reading its own run), and in runs for the compaction.
 // ---------------------------------------------------------------------------
 template <int KPT>
 __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__restrict__ keys_all,
@@ -365,12 +367,14 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
 #pragma unroll
         for (int i = 0; i < KPT; ++i) kreg[i] = (j0 + i < j1) ? keys[j0 + i] : 0ull;
     }
+    int cnt = int(j1 > j0 ? j1 - j0 : 0);
     // f(i, key) for the thread's columns j0 + i, in order
     auto each = [&](auto f) {
+        asm volatile("" : "+v"(cnt));  // (the comparisons are cheap: not kept in registers from pass to pass)
         if constexpr (KPT > 0) {
 #pragma unroll
             for (int i = 0; i < KPT; ++i)
-                if (j0 + i < j1) f(i, kreg[i]);
+                if (i < cnt) f(i, kreg[i]);
         } else {
             for (int64_t j = j0; j < j1; ++j) f(int(j - j0), keys[j]);
         }
@@ -386,7 +390,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
         for (int b = t; b < 256; b += TOPK_THREADS) hist[b] = 0u;
         __syncthreads();
         const unsigned long long prefix = s_prefix;
-        each([&](int, unsigned long long u) {
+        auto count = [&](int, unsigned long long u) {
             if ((u & mask) != prefix) return;
             const uint32_t bin = uint32_t(u >> shift) & 255u;
             const uint32_t first = __builtin_amdgcn_readfirstlane(bin);
@@ -396,7 +400,13 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
             } else {
                 atomicAdd(&hist[bin], 1u);
             }
-        });
+        };
+        if constexpr (KPT > 0) {
+            each(count);
+        } else {  // (any order counts: neighbouring lanes read neighbouring keys)
+#pragma unroll 4
+            for (int64_t j = t; j < d_in; j += TOPK_THREADS) count(0, keys[j]);
+        }
         __syncthreads();
         // the digit holding the rem-th largest key: with cum(dgt) the count of
         // keys in digits above dgt, the unique dgt with cum < rem <= cum + h.
@@ -453,7 +463,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
     {
         int r = eq_rank;
         each([&](int i, unsigned long long u) {
-            const int64_t j = j0 + i;
+            const uint32_t j = uint32_t(j0) + uint32_t(i);
             const unsigned long long um = u & mask;
             const bool sel = (um > T) || (um == T && r < need_eq);
             if (um == T) ++r;
@@ -472,19 +482,17 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const double *__rest
     for (int64_t w = t; w < words; w += TOPK_THREADS) bitmap[w] = s_bits[w];
 }
 
+// The smallest register run that holds the keys (an encode of 64 x 12288 in 35
+// us, in runs of 32 38; of 64 x 25600 in 73, read again for every digit 95).
 hipError_t launch_topk(int64_t n_mats, const double *keys, const float *absmax, int64_t n, int64_t k, int64_t words,
                        float pmax, int32_t *idx, float *scale, int32_t *colmap, uint32_t *bitmap, hipStream_t st)
 {
-    const dim3 grid(unsigned(n_mats), 1u, 1u), blk(TOPK_THREADS);
-    if (n <= 8 * TOPK_THREADS)
-        hipLaunchKernelGGL(topk_kernel<8>, grid, blk, size_t(words) * 4, st, keys, absmax, n, k, words, pmax, idx, scale,
-                           colmap, bitmap);
-    else if (n <= 32 * TOPK_THREADS)
-        hipLaunchKernelGGL(topk_kernel<32>, grid, blk, size_t(words) * 4, st, keys, absmax, n, k, words, pmax, idx,
-                           scale, colmap, bitmap);
-    else
-        hipLaunchKernelGGL(topk_kernel<0>, grid, blk, size_t(words) * 4, st, keys, absmax, n, k, words, pmax, idx, scale,
-                           colmap, bitmap);
+    const auto kernel = (n <= 8 * TOPK_THREADS)    ? topk_kernel<8>
+                        : (n <= 16 * TOPK_THREADS) ? topk_kernel<16>
+                        : (n <= 32 * TOPK_THREADS) ? topk_kernel<32>
+                                                   : topk_kernel<0>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(n_mats)), dim3(TOPK_THREADS), size_t(words) * 4, st, keys, absmax, n, k, words,
+                       pmax, idx, scale, colmap, bitmap);
     return hipGetLastError();
 }
 
