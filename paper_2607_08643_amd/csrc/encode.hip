@@ -91,14 +91,17 @@ __global__ __launch_bounds__(256) void colscore_kernel(const T *__restrict__ W, 
 // lane per column: there a wave has its own 64 rows (8 KiB) in flight and
 // converts, squares and compares between its loads (12288 x 4096 bf16, 64
 // waves: 261 us). Here a workgroup owns 64 columns and its eight waves take
-// 8 KiB tiles of the rows in turn. A wave brings its next two tiles to LDS by
-// DMA and reads, converts and compares a tile ahead of its turn; in its turn it
-// takes the 64 running sums from LDS, adds the tile, one fp64 fma a row (1.9
-// ns; with the conversion in the chain it would be 5.3), and hands the sums on.
-// The square of a bf16 or fp32 value is exact in fp64, so the fma rounds once,
-// as the separate product and sum do; rows past d_out are zeros, which change
-// neither the sum nor the absmax. Every wave of a workgroup is resident and
-// reaches each of its turns, so the wait for a turn ends.
+// tiles of the rows (10 KiB: 80 of bf16, 40 of fp32) in turn. A wave has one
+// slot of LDS: its tile is there by DMA when it begins, it reads, converts and
+// compares the tile ahead of its turn, then requests its next tile into the
+// slot, which arrives while it waits for its turn and takes it, and while the
+// other seven take theirs. In its turn it takes the 64 running sums from LDS,
+// adds the tile, one fp64 fma a row (1.9 ns; with the conversion in the chain
+// it would be 5.3), and hands the sums on. The square of a bf16 or fp32 value
+// is exact in fp64, so the fma rounds once, as the separate product and sum
+// do; rows past d_out are zeros, which change neither the sum nor the absmax.
+// Every wave of a workgroup is resident and reaches each of its turns, so the
+// wait for a turn ends.
 constexpr int SCT_WAVES = 8, SCT_SLOT = 80 * 128;
 
 template <typename T>
@@ -198,7 +201,8 @@ __global__ __launch_bounds__(64 * SCT_WAVES) void colscore_turns_kernel(const T 
         __builtin_amdgcn_s_setprio(0);
     }
     s_max[wave][lane] = mx;
-    __syncthreads();  // (and no DMA is in flight into LDS past here)
+    __builtin_amdgcn_s_waitcnt(0);  // no DMA of this wave is in flight into LDS past here
+    __syncthreads();
     const int64_t col = col0 + lane;
     if (wave != 0 || col >= d_in) return;
     double s = s_sum[lane];
@@ -954,11 +958,25 @@ size_t select_ws_layout(int64_t d_ffn, char *base, SelectWs *ws)
 
 namespace {
 
-// Up to this many 64-column groups the turns kernel is the faster one: 512
-// groups of 12288 rows 522 against 602 us for the whole encode, 2304 groups of
-// 4096 rows 752 against 766, 3072 groups of 4096 rows 1037 against 975 (there
-// one lane per column already keeps 12 waves a compute unit in flight).
-constexpr int64_t COLSCORE_TURNS_MAX_BLOCKS = 2560;
+// Whether the turns kernel is the faster one for this many 64-column groups. It
+// runs one workgroup per compute unit; with more groups, one lane per column keeps
+// enough waves in flight, the sooner the fewer rows there are to hide the
+// turns' start behind and the more rows a tile holds (bf16). Whole encodes in
+// us, one lane per column -> turns, of 12 / 20 / 28 stacked matrices of 4096
+// columns (768, 1280, 1792 groups):
+//   bf16:  128 rows 35 -> 34, 39 -> 41, 40 -> 48; 512 rows 52 -> 51, 73 -> 73,
+//          86 -> 95; 4096 rows 241 -> 225, 377 -> 369, 498 -> 525;
+//   fp32:  128 rows 38 -> 35, 42 -> 42, 48 -> 52; 512 rows 69 -> 61, 100 -> 89,
+//          119 -> 117; 4096 rows 357 -> 353, 624 -> 578, 811 -> 828.
+// With many rows of fp32 it stays ahead where its rounds are full (512 rows, 9
+// and 7.5 rounds: 152 -> 149, 145 -> 148; 2048 rows 547 -> 536, 474 -> 494).
+// Below 64 rows both take the same time for few groups (16 rows: 20 us).
+constexpr bool colscore_turns_pay(int64_t blocks, int64_t d_out, bool bf16)
+{
+    const int64_t rounds = (blocks + 255) / 256;
+    if (!bf16 && d_out >= 512 && rounds <= 10 && 256 * rounds - blocks <= 64) return true;
+    return rounds <= ((d_out < 64) ? 1 : bf16 ? (d_out < 512 ? 3 : 5) : (d_out < 256 ? 4 : 6));
+}
 
 template <typename T>
 hipError_t launch_colscore(const void *W, int64_t n_mats, int64_t d_out, int64_t d_in, const float *g, double *keys,
@@ -966,7 +984,7 @@ hipError_t launch_colscore(const void *W, int64_t n_mats, int64_t d_out, int64_t
 {
     const int64_t blocks = (d_in + 63) / 64 * n_mats;
     // (it loads whole 16-byte units of rows that are there: none of an empty matrix)
-    if (d_out > 0 && d_out < (int64_t(1) << 30) && d_in * int64_t(sizeof(T)) % 16 == 0 && blocks <= COLSCORE_TURNS_MAX_BLOCKS) {
+    if (d_out > 0 && d_out < (int64_t(1) << 30) && d_in * int64_t(sizeof(T)) % 16 == 0 && colscore_turns_pay(blocks, d_out, sizeof(T) == 2)) {
         constexpr int lds = SCT_WAVES * SCT_SLOT;
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&colscore_turns_kernel<T>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
