@@ -219,8 +219,9 @@ SPLITK = [
     ("splitk-200x2600-d8", 200, 2600, dict(d=8, hidden=8), torch.bfloat16, 1, False),
     ("splitk-130x2608-d16", 130, 2608, dict(d=16, hidden=16), torch.bfloat16, 1, False),
 ]
-# Stage counts 1 and 3 at d = 8 and 3 and 4 at d = 16, so that every kernel
-# shape of the GEMM (token tile x row block x stages) runs at some M.
+# Stage counts 1 and 3 at d = 8 and 3 and 4 at d = 16, so that the 16- and
+# 64-token tiles run at every stage count (the larger tiles: in the tests of the
+# decode-once product, which most of these shapes take above 64 or 256 tokens).
 GEMM_STAGES = [
     ("mlp-3stage-70x1000-d8", 70, 1000, dict(d=8, hidden=8, stages=3), torch.bfloat16, 1, False),
     ("mlp-4stage-90x640-d16", 90, 640, dict(d=16, hidden=16, stages=4), torch.bfloat16, 1, False),
@@ -433,8 +434,9 @@ def test_full_size_encode_and_gemv(case, gpu):
 @pytest.mark.parametrize("d", [8, 16])
 def test_full_size_gemm(d, M, gpu):
     """Qwen3-8B o_proj shape at the batched sizes of the workload, with the
-    rank-16 LoRA (token tiles of 16, 64 and 128; at M = 16 and 64 the K steps
-    are split over several blocks, whose partials a second launch adds)."""
+    rank-16 LoRA (token tiles of 16 and 64, whose K steps are split over
+    several blocks and their partials added by a second launch; at M = 256 the
+    weights decoded once)."""
     say(f"qwen3-8b o_proj 4096x4096 gemm M={M} d={d}")
     cfg = bsq.Config(d=d, hidden=d)
     oc = ocfg(cfg)
@@ -459,10 +461,10 @@ def test_full_size_gemm(d, M, gpu):
 
 @pytest.mark.parametrize("d_out,d_in,M", [(2304, 4608, 64), (512, 1024, 300)], ids=["2304x4608-M64", "512x1024-M300"])
 def test_gemm_wide_and_long_shapes(d_out, d_in, M, gpu):
-    """The d = 8 shapes no other case selects: 64-token tiles of 128-row
-    blocks (more than 4096 inputs, at most 64 tokens, two blocks per compute
-    unit) and 128-token tiles of 64-row blocks (at most 2048 rows, more than
-    256 tokens), with rank-16 LoRA and 1% protected columns."""
+    """64-token tiles of 128-row blocks at d = 8 (more than 4096 inputs, at most
+    64 tokens, two blocks per compute unit), which no other case selects, and a
+    small product of more than 256 tokens, decoded once; rank-16 LoRA and 1%
+    protected columns."""
     say(f"gemm {d_out}x{d_in} M={M} d=8")
     cfg = bsq.Config(d=8, hidden=8)
     oc = ocfg(cfg)
