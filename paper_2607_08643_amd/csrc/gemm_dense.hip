@@ -24,6 +24,7 @@
 // come kp32 / 32 units of protected positions, two of the adapter (hi | mid,
 // lo | 0), and a zero unit where KU would be odd.
 #include <algorithm>
+#include <atomic>
 
 #include "gemm_common.h"
 
@@ -579,9 +580,13 @@ template <int MF, int NF, int WM, int WN>
 hipError_t launch_product(DenseArgs a, hipStream_t st)
 {
     using G = DenseShape<MF, NF, WM, WN>;
-    static const hipError_t lds = hipFuncSetAttribute(reinterpret_cast<const void *>(&dense_gemm<MF, NF, WM, WN>),
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(G::LDS));
-    if (lds != hipSuccess) return lds;
+    static std::atomic<bool> lds_set{false};  // the ring exceeds the default dynamic LDS limit
+    if (!lds_set.load(std::memory_order_relaxed)) {  // (a call that failed here leaves it to the next)
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&dense_gemm<MF, NF, WM, WN>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(G::LDS));
+        if (e != hipSuccess) return e;
+        lds_set.store(true, std::memory_order_relaxed);
+    }
     a.ntiles = int((a.rows + G::BN - 1) / G::BN);
     hipLaunchKernelGGL((dense_gemm<MF, NF, WM, WN>), dim3(unsigned(a.mtiles) * unsigned(a.ntiles) * unsigned(a.ksplit)), dim3(64 * G::NW), G::LDS, st, a);
     return hipGetLastError();
