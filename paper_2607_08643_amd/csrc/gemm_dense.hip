@@ -345,7 +345,10 @@ struct DenseShape {
     static constexpr int XU = MF * WM, WU = NF * WN;   // units per step
     static constexpr int BM = 16 * XU, BN = 16 * WU;
     static constexpr int SLOT = (XU + WU) * 1024;
-    // the 128 x 128 block runs two per compute unit, five slots each
+    // five slots for the 128 x 128 block, half a compute unit's LDS. (One runs
+    // per compute unit all the same: the kernel's register count is raised to
+    // the two waves per SIMD that it asks for, and the plan's step time for
+    // this tile was measured so.)
     static constexpr int NS_FIT = GEMM_LDS_BYTES / (XU + WU <= 16 ? 2 : 1) / SLOT;
     static constexpr int NS = NS_FIT < 6 ? NS_FIT : 6;
     static constexpr int NI = XU + WU;                 // DMA instructions per step: wave w issues w, w + NW, ...

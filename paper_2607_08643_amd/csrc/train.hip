@@ -8,7 +8,7 @@
 //
 // Parameters are one fp32 vector theta = E [b][d] | W1 [h][b] | b1 [h] |
 // W2 [d][h] | b2 [d]. Every reduction runs in a fixed order that depends on n
-// alone, so a step gives the same bits on every run:
+// and on d, b and h alone, so a step gives the same bits on every run:
 //   1. train_bits_kernel: per chunk z, u and the bit probabilities
 //      s_ij = sigma(2 tau u_ij / sqrt(b)); per block the sums of s and of the
 //      per-chunk entropies;
@@ -411,10 +411,13 @@ __global__ __launch_bounds__(TB) void train_sum_kernel(const TrainArgs a)
         }
         return;
     }
-    // The entropy partials are added one after the other. L_ent is the small
-    // difference of two entropies near b ln 2, so the order of this sum shows
-    // in the loss (in a tree it moved by 6e-5 of itself at 131,072 chunks,
-    // b = 16): 512 additions from LDS, beside the other blocks' sums.
+    // The entropy partials, up to 1,024, are added one after the other in fp32,
+    // which keeps the reported loss what it was when every block had its own
+    // partial. It is not the most exact order: L_ent is the small difference of
+    // two entropies near b ln 2, and the chain's rounding shows in it (65,536
+    // chunks, b = 8: up to 9e-5 of L_ent from its 64-bit value; 131,072 chunks,
+    // b = 16: 1e-3, 5e-6 to 2e-5 of the loss; in a tree of the same partials
+    // 3e-5 and less). The gradient does not depend on it.
     __shared__ float s_h[BITS_BLOCKS];
     float v[2] = {0.0f, 0.0f};  // reconstruction, commitment
     for (int64_t k = t; k < a.nback; k += TB) {
